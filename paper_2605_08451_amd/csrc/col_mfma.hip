@@ -61,8 +61,11 @@ typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ uint32_t pack_h2(float re, float im) {
-    const __half2 h = __float22half2_rn(make_float2(re, im));
-    return __builtin_bit_cast(uint32_t, h);
+    // (the empty asm statement keeps the pair in one register: seen through, its halves would
+    // be converted and carried apart)
+    uint32_t w = h2_bits(re, im);
+    asm("" : "+v"(w));
+    return w;
 }
 __device__ __forceinline__ uint32_t pack_bf2(float re, float im) { return bf2_bits(re, im); }
 
@@ -196,7 +199,7 @@ __device__ __forceinline__ uint32_t col_fwd_task(const void* __restrict__ src, i
     // per-document twiddle w_P^(u j) = w_P^(k1 j) * w_P^(16 k2 j), u = k1 + 16 k2: the first
     // factor goes into this column's stage-1 matrix (row k1 = lane % 16), the second has
     // four values per lane (k2 = 4 r2 + h)
-    const __amdgpu_buffer_rsrc_t rt = doc_buffer(t.tw + sg->twf_off, static_cast<uint32_t>(sg->P) * 8);
+    const __amdgpu_buffer_rsrc_t rt = doc_buffer(t.tw + __builtin_amdgcn_readfirstlane(sg->twf_off), static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(sg->P)) * 8);
     const auto wk = __builtin_amdgcn_raw_buffer_load_b64(rt, p * j * 8, 0, 0);
     u2 twq[4];
 #pragma unroll
@@ -211,7 +214,7 @@ __device__ __forceinline__ uint32_t col_fwd_task(const void* __restrict__ src, i
 
     uint32_t tw_lane[4];  // complex fp16
 #pragma unroll
-    for (int r2 = 0; r2 < 4; ++r2) tw_lane[r2] = h2_bits(__uint_as_float(twq[r2][0]), __uint_as_float(twq[r2][1]));
+    for (int r2 = 0; r2 < 4; ++r2) tw_lane[r2] = pack_h2(__uint_as_float(twq[r2][0]), __uint_as_float(twq[r2][1]));
     // both table factors carry 1/sqrt(N1): undo one (x 16, exact)
     const float wmul = IN == kBf16In ? 16.0f * glob_x : 16.0f;
     const float2 w1 = make_float2(__uint_as_float(wk[0]) * wmul, __uint_as_float(wk[1]) * wmul);
@@ -245,6 +248,9 @@ __device__ __forceinline__ uint32_t col_fwd_task(const void* __restrict__ src, i
                 if constexpr (AMAX) am = amax_pk(amax_pk(amax_pk(amax_pk(am, b[0]), b[1]), b[2]), b[3]);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) y[n2][r] = pack_h2(dre[r], dim[r]);
+                // (accumulators of a few n2 at a time: without AMAX's chain more would be live, and spill)
+                if constexpr (!AMAX)
+                    if (n2 % 2 == 1) __builtin_amdgcn_sched_barrier(0);
             }
         } else {
             const u4 are = {hi[0], hi[1], lo[0], lo[1]}, aim = imag_words(are);
@@ -297,7 +303,7 @@ __device__ __forceinline__ uint32_t col_fwd_task(const void* __restrict__ src, i
             // register r2 of lane (p, h) is grid row k1 + 16 (4 r2 + h), pair p
 #pragma unroll
             for (int r2 = 0; r2 < 4; ++r2)
-                __builtin_amdgcn_raw_buffer_store_b32(cmul_h2(h2_bits(dre[r2], dim[r2]), tw_lane[r2]), rg,
+                __builtin_amdgcn_raw_buffer_store_b32(cmul_h2(pack_h2(dre[r2], dim[r2]), tw_lane[r2]), rg,
                                                       static_cast<int>(st_lane[r2]), 0, 0);
         }
     }
@@ -455,7 +461,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
         const uint32_t tk = static_cast<uint32_t>(__builtin_amdgcn_readlane(tk_all, k1));
         u4 b;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) b[i] = cmul_h2_s(yg[k1][i], tk);
+        for (int i = 0; i < 4; ++i) b[i] = cmul_h2(yg[k1][i], tk);
         const f4 dre = mma_f16(are1, b, zero);
         const f4 dim = mma_f16(aim1, b, zero);
 #pragma unroll

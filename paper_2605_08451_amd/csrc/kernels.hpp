@@ -115,7 +115,7 @@ constexpr int partner_tab_u4(int nb) { return (nb * nb * 64 + partner_pre_u4(nb)
 // over the first document's rows (the others are left as they were); with sum, dscale
 // (a power of two) multiplies the data rows' spectra before they are rounded to fp16,
 // and out2 writes the inverse over the first document's second-grid rows instead, which
-// leaves the grid itself as it was (both: 1 and false without sum).
+// leaves the grid itself as it was (both: 1 and false without sum); sum takes corr = 1 only.
 hipError_t launch_row_groups(int max_nb, void* grid, int64_t grid_pb_stride, const void* fgrid,
                              int64_t fgrid_pb_stride, const Seg* segs, const int32_t* docs, const RowGroup* groups,
                              const int32_t* blocks, int nblocks, const void* tabs, int npb, int corr,
