@@ -124,6 +124,8 @@ typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kTab2 = 16 * 2 * 64;  // stage-2 operands: 16 matrices x (re, im) x 64 lanes
 
+constexpr float kFoldMin = 1.0f / kMaxScaleGuess, kFoldMax = kMaxScaleGuess;
+
 constexpr int kF16In = 0;   // fp16 channel pairs (filter taps, packed by the pair transpose)
 constexpr int kBf16In = 1;  // bf16 channel pairs (x): used as bf16 operands as loaded
 
@@ -164,6 +166,10 @@ __device__ __forceinline__ u4 imag_words(u4 a) {
 // the grid hold tokens too (a document longer than half its transform, i.e. than the filter);
 // otherwise their loads and half of the stage-1 contraction are left out.  Returns the
 // lane's largest bf16 magnitude bits with AMAX.
+// The stage-1 matrix carries the range scale glob_x within kFoldMin .. kFoldMax, where
+// the bf16 halves of its entries are normal numbers; what a scale past them (x below 1e-17 or
+// above 1e18) leaves over multiplies the loaded bf16 pairs themselves, a power of two that
+// takes them towards 1 (with AMAX, whose scale is a guess, the guess stays in that range).
 template <int IN, bool AMAX, bool FULL>
 __device__ __forceinline__ uint32_t col_fwd_task(const void* __restrict__ src, int64_t src_row_stride, int D,
                                                  uint32_t* __restrict__ grid, int64_t grid_pb_stride,
@@ -215,8 +221,22 @@ __device__ __forceinline__ uint32_t col_fwd_task(const void* __restrict__ src, i
     uint32_t tw_lane[4];  // complex fp16
 #pragma unroll
     for (int r2 = 0; r2 < 4; ++r2) tw_lane[r2] = pack_h2(__uint_as_float(twq[r2][0]), __uint_as_float(twq[r2][1]));
+    float fold = 1.0f;
+    if constexpr (IN == kBf16In) {
+        fold = AMAX ? glob_x : fminf(fmaxf(glob_x, kFoldMin), kFoldMax);
+        if constexpr (!AMAX)
+            if (glob_x != fold) {  // wave-uniform
+                const float rest = glob_x / fold;
+#pragma unroll
+                for (int n2 = 0; n2 < 16; ++n2)
+#pragma unroll
+                    for (int i = 0; i < (FULL ? 4 : 2); ++i)
+                        xb[n2][i] = pack_bf2(__uint_as_float(xb[n2][i] << 16) * rest,
+                                             __uint_as_float(xb[n2][i] & 0xffff0000u) * rest);
+            }
+    }
     // both table factors carry 1/sqrt(N1): undo one (x 16, exact)
-    const float wmul = IN == kBf16In ? 16.0f * glob_x : 16.0f;
+    const float wmul = 16.0f * fold;
     const float2 w1 = make_float2(__uint_as_float(wk[0]) * wmul, __uint_as_float(wk[1]) * wmul);
     float2 a1[4];
     a1[0] = cmul(make_float2(__uint_as_float(e01[0]), __uint_as_float(e01[1])), w1);

@@ -136,6 +136,9 @@ constexpr int kMtFwd2 = 256;       // forward stage 2 per k1: re, im
 constexpr int kMtInv2 = 2304;      // inverse stage 2 per n2: re, im
 constexpr int kMtEntries = 4352;
 
+// first_scale of a pass with amax_out: a power of two from 1 / kMaxScaleGuess to kMaxScaleGuess
+constexpr float kMaxScaleGuess = 0x1p60f;
+
 // src_dtype 1: bf16 channels [rows][N][D] (x); 0: fp16 channel pairs [taps][D / 2] from
 // launch_transpose_pairs (filter taps).
 // amax_out (bf16 sources only; null for none): per column task, the largest bf16 magnitude

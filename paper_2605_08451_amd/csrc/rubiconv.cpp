@@ -447,10 +447,10 @@ int hint_slot(int kind, const void* input) {
 }
 
 // The scale a call's first column pass starts at: the last one its plan found for the
-// slot (a power of two in the range pow2_scale gives, else 1).
+// slot (a power of two in the first pass's range, else 1).
 float scale_guess(const rubiconv_plan_s* plan, int slot) {
     const float g = reinterpret_cast<const volatile float*>(plan->scale_hint)[slot];
-    return g >= 0x1p-126f && g <= 0x1p127f ? g : 1.0f;
+    return g >= 1.0f / rubiconv::kMaxScaleGuess && g <= rubiconv::kMaxScaleGuess ? g : 1.0f;
 }
 
 // The forward column pass of `in` into `grid` (and the long rows' first level); with

@@ -256,3 +256,51 @@ def test_scale_found_in_the_column_pass(device, monkeypatch, lens, d, y_dtype):
         v = dyv[0, sum(lens[:-1]):, where]
         bar = min(0.5, 5e-3 * (np.linalg.norm(v) / abs(v[-1]) if where else 1.0))
         assert rel_l2(dk, oracle.grad_k(W.x, dyv, W.cu_seqlens, W.L, threads=ORACLE_THREADS)) <= bar, (d, where)
+
+
+@pytest.mark.parametrize("L", [64, 341])
+@pytest.mark.parametrize("y_dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("scale", [3e-38, 1e-20, 1e20, 1e35])
+def test_scales_at_the_ends_of_the_type(device, monkeypatch, scale, y_dtype, L):
+    """Inputs (and upstream gradients) whose range scale nearly leaves float32's exponents, on
+    the matrix-core column pass, whose matrices carry that scale: full and half-filled columns
+    (documents longer and no longer than the filter), a first call, whose guess is wrong, and a
+    second one, the same bits.  Bar 5e-3, twice the fp16 grids' and the bf16 output's 2e-3: a
+    matrix that has lost its entries' lower halves gives 2e-3 more, an overflowing one NaN."""
+    import torch
+    import paper_2605_08451_amd as rc
+    from tests.common import rel_l2
+    monkeypatch.setenv("RUBICONV_DIRECT_MAX", "0")
+    W0 = wl.make_case([[300, 41], [341]], D=D, L=L, x_dtype="bf16", seed=L)
+    rng = np.random.default_rng(L)
+
+    def at(s):
+        v = wl.round_to_bf16((s * rng.standard_normal(W0.x.shape)).astype(np.float32))
+        return v.astype(np.float64), torch.from_numpy(v.astype(np.float32)).to(torch.bfloat16).to(device)
+
+    k = torch.from_numpy(W0.filters).to(device)
+    plan = rc.Plan(W0.cu_seqlens, N=W0.N, D=D, L=L, x_dtype="bf16", y_dtype=y_dtype)
+    spec = rc.filter_spectrum(plan, k)
+    (loud, loud_t), (one, one_t) = at(scale), at(1.0)
+    yt = {"bf16": torch.bfloat16, "f32": torch.float32}[y_dtype]
+
+    def check(name, call, ref):
+        first, second = call(), call()
+        torch.cuda.synchronize()
+        got = first.float().cpu().numpy().astype(np.float64)
+        assert np.isfinite(got).all(), (name, scale)
+        s = 1.0 / np.abs(ref).max()
+        assert rel_l2(got * s, ref * s) <= 5e-3, (name, scale, rel_l2(got * s, ref * s))
+        assert torch.equal(first, second), (name, scale)
+
+    gx = oracle.grad_x(W0.filters, loud, W0.cu_seqlens, threads=ORACLE_THREADS)
+    check("y", lambda: rc.packed_conv(plan, loud_t, spec),
+          oracle.conv_direct(loud, W0.filters, W0.cu_seqlens, threads=ORACLE_THREADS))
+    check("dx", lambda: rc.packed_conv_dx(plan, loud_t.to(yt), spec), gx)
+    check("dk of dy", lambda: rc.packed_conv_dk(plan, one_t, loud_t.to(yt)),
+          oracle.grad_k(one, loud, W0.cu_seqlens, L, threads=ORACLE_THREADS))
+    check("dk of x", lambda: rc.packed_conv_dk(plan, loud_t, one_t.to(yt)),
+          oracle.grad_k(loud, one, W0.cu_seqlens, L, threads=ORACLE_THREADS))
+    check("fused dx", lambda: rc.packed_conv_backward(plan, one_t, loud_t.to(yt), spec)[0], gx)
+    check("fused dk", lambda: rc.packed_conv_backward(plan, one_t, loud_t.to(yt), spec)[1],
+          oracle.grad_k(one, loud, W0.cu_seqlens, L, threads=ORACLE_THREADS))
