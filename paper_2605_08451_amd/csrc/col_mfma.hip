@@ -223,10 +223,11 @@ __device__ __forceinline__ uint32_t col_fwd_task(const void* __restrict__ src, i
     for (int r2 = 0; r2 < 4; ++r2) tw_lane[r2] = pack_h2(__uint_as_float(twq[r2][0]), __uint_as_float(twq[r2][1]));
     float fold = 1.0f;
     if constexpr (IN == kBf16In) {
-        fold = AMAX ? glob_x : fminf(fmaxf(glob_x, kFoldMin), kFoldMax);
+        const float scale = glob_x * sg->in_scale;
+        fold = AMAX ? scale : fminf(fmaxf(scale, kFoldMin), kFoldMax);
         if constexpr (!AMAX)
-            if (glob_x != fold) {  // wave-uniform
-                const float rest = glob_x / fold;
+            if (scale != fold) {  // wave-uniform
+                const float rest = scale / fold;
 #pragma unroll
                 for (int n2 = 0; n2 < 16; ++n2)
 #pragma unroll
@@ -453,7 +454,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
                                             rt, static_cast<int>(16u * (4 * i + h) * j * 8), 0, 0));
     const u4 e01 = mt[kMtInv1 + lane], e23 = mt[kMtInv1 + 64 + lane];  // w16^(-n2 k2), n2 = lane % 16, k2 = 4 i + h
     // undoes the range scales of this lane's pair on the fp32 outputs
-    const float out_mul = sc.pair[pb * kPairsPerBlock + p].y * sc.glob->y;
+    const float out_mul = sc.pair[pb * kPairsPerBlock + p].y * sc.glob->y * sg->out_scale;
     __builtin_amdgcn_sched_barrier(0);
 
     // the k2 part of the conjugate twiddle goes into this column's stage-1 matrix; the k1

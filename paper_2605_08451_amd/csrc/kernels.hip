@@ -218,7 +218,7 @@ __global__ __launch_bounds__(16 * R) void col_fwd_kernel(const void* __restrict_
 
     const float2* twf = t.tw + sg->twf_off;
     G* out = grid + pb * grid_pb_stride + (sg->grid_off + j) * kPairsPerBlock + p;
-    const float mul = sc.pair[pb * kPairsPerBlock + p].x * (FOLD ? glob : sc.glob->x);
+    const float mul = sc.pair[pb * kPairsPerBlock + p].x * (FOLD ? glob : sc.glob->x) * sg->in_scale;
 #pragma unroll
     for (int k2 = 0; k2 < R; ++k2) {
         const int u = q + R * k2;
@@ -259,7 +259,7 @@ __global__ __launch_bounds__(16 * R) void col_inv_kernel(const G* __restrict__ g
 #pragma unroll
     for (int k1 = 0; k1 < R; ++k1) v[k1] = lds[k1 * LD + q * 16 + p];  // thread q holds n2 = q
     Dft<R, 1>::run(v);  // over k1 -> n1
-    const float mul = sc.pair[pb * kPairsPerBlock + p].y * sc.glob->y;
+    const float mul = sc.pair[pb * kPairsPerBlock + p].y * sc.glob->y * sg->out_scale;
 #pragma unroll
     for (int n1 = 0; n1 < R; ++n1) v[n1] = cscale(v[n1], mul);
 

@@ -99,8 +99,7 @@ hipError_t launch_row_reg(void* grid, int64_t grid_pb_stride, const void* fgrid,
 // inverse takes their conjugates); the partner row's input twiddles w^j, for rows of up to
 // kTwinBlocks blocks folded into a second set of operands, for longer ones as 16 nb complex
 // fp16 factors w^(-j); 16 nb complex fp32 twiddles kappa w^j, then kappa (the inverse's scale
-// over the operands'), g (the filter spectra's), c (a class sum's spectra's) and ic (its
-// inverse's over kappa), fp32; padded to whole 1 KB chunks.
+// over the operands'), fp32; padded to whole 1 KB chunks.
 constexpr int partner_pre_u4(int nb) { return nb <= kTwinBlocks ? nb * nb * 64 : 4 * nb; }
 constexpr int partner_tab_u4(int nb) { return (nb * nb * 64 + partner_pre_u4(nb) + 8 * nb + 1 + 63) / 64 * 64; }
 

@@ -74,6 +74,10 @@ struct Seg {
     int8_t fac[kMaxFactors];
     int8_t pad_[2];
     int32_t dense_off; // matrix-core row pass: first 16-byte entry of the class's DFT operands
+    // powers of two on the forward column pass's results (a document's rows' row_gain, 1 for a
+    // filter class) and on the inverse's (1; in the filter gradient's table 1 / row_gain)
+    float in_scale = 1.0f;
+    float out_scale = 1.0f;
 };
 static_assert(sizeof(Seg) % 8 == 0, "Seg must stay 8-byte aligned in arrays");
 

@@ -97,6 +97,9 @@ void build_mfma_tables(std::vector<uint32_t>* out);
 // s w_m^(-k j), s a power of two near 1 / sqrt(m), zero outside k, j < m; the inverse is kappa
 // times its conjugate), then the partner-row twiddles (kernels.hpp: partner_tab_u4).
 void build_partner_tables(int m, int n1, std::vector<uint32_t>* out);
+// The power of two (1 or 2) that the grids of documents with rows of m points carry, so that
+// with the operands' s their spectra are not below 1 / sqrt(m).
+double row_gain(int m);
 // Batched rows (m <= kMaxBatchM): the same tables in block-diagonal form for 16 / m rows
 // side by side (row r at points r m .. r m + m - 1).
 void build_batch_tables(int m, int n1, std::vector<uint32_t>* out);
