@@ -249,11 +249,13 @@ rubiconv_status_t rubiconv_packed_conv_noalloc(rubiconv_plan_t plan, const void*
  * document's own grid, the inverse leaves the document's cross-correlation at
  * lags 0..len-1, and the documents' correlations are summed per channel and lag.
  * The inverse transforms are linear and the same for all documents of one size
- * class, so on the matrix-core row pass (bf16 inputs, rows of at most 128 points) and for
- * float32 rows of at most 8 points the products of up to eight documents of a class are added first, longest
+ * class, so on the matrix-core row pass (bf16 inputs, rows of at most 128 points) the
+ * products of up to eight documents of a class are added first, longest
  * document first, and transformed back once, onto the longest one's positions:
  * the class's transform size keeps the causal padding of its longest document,
  * so no document's correlation wraps onto a lag below that document's length.
+ * Float32 rows of at most 8 points do the same for documents of one number of lags
+ * (min(length, L)), so that a lag holds the rounding of the documents that have it only.
  */
 
 /*

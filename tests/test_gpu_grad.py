@@ -451,3 +451,29 @@ def test_dk_small_products(device, n, m, D):
     ref = oracle.grad_k(W.x, dyv, W.cu_seqlens, W.L)
     e = np.linalg.norm(dk - ref) / np.linalg.norm(ref)
     assert e <= 2.65e-3, (n, D, e)
+
+
+@pytest.mark.parametrize("m", [2, 8])
+def test_float_class_sums_keep_lags_apart(device, monkeypatch, m):
+    """dk at a lag is a sum over the documents long enough to have it: in float32 a shorter
+    document of the same size class, 1e6 times as loud or holding a NaN, leaves the longer
+    one's last lags as they are.  Bar 2e-6 there, as for the other float32 sums (a class sum
+    of the two gave 0.2 and more, or NaN)."""
+    import torch
+    import paper_2605_08451_amd as rc
+    monkeypatch.setenv("RUBICONV_DIRECT_MAX", "0")
+    n1, n2 = 128 * m, 128 * m - 40
+    W = wl.make_case([[n2, n1, n2, n1, n1]], D=6, L=3 * n1, x_dtype="f32", seed=m)
+    dyv, dy = _dy(W, m + 1)
+    x = W.x.astype(np.float32).copy()
+    x[0, :n2] *= 1e6
+    plan = rc.Plan(W.cu_seqlens, N=W.N, D=W.D, L=W.L, x_dtype="f32")
+    assert set(plan.doc_table()[:, 4]) == {m}
+    dk = rc.packed_conv_dk(plan, torch.from_numpy(x).to(device), dy.to(device)).cpu().numpy().astype(np.float64)
+    ref = oracle.grad_k(x.astype(np.float64), dyv, W.cu_seqlens, W.L)
+    assert rel_l2(dk, ref) <= 2e-6
+    assert rel_l2(dk[:, n2:n1], ref[:, n2:n1]) <= 2e-6, rel_l2(dk[:, n2:n1], ref[:, n2:n1])
+    x[0, 3] = np.nan
+    bad = rc.packed_conv_dk(plan, torch.from_numpy(x).to(device), dy.to(device)).cpu().numpy()
+    assert np.isnan(bad[:, :n2 - 3]).any(axis=0).all()
+    np.testing.assert_array_equal(bad[:, n2:], dk[:, n2:].astype(np.float32))
