@@ -102,12 +102,22 @@ namespace {
 constexpr size_t kAlign = 256;
 // A fork to a side stream and the join back cost the host about 25 us and leave the GPU some
 // 20 us with nothing running, so launches go to side streams only where they are long enough
-// to fill that: the direct path from kForkDirect token-channels on (measured per step, fork
-// against one stream: 0.2 M 54 against 36 us, 4.2 M 177 against 191, 8 M 158 against 171),
-// the row stage's launches, where it has several (fp32 grids), from kForkRowPoints grid points
-// times pairs on (3 M 107 against 85 us, 14 M 189 against 185).
+// to fill that.  The direct path from kForkDirect token-channels on (measured per step, fork
+// against one stream: 0.2 M 54 against 36 us, 4.2 M 177 against 191, 8 M 158 against 171).
+// The row stage's launches, where it has several, by its grid points times pairs (measured,
+// us per convolution, one stream / forked):
+//   float32, three and more (a launch per size class): 4.7 M 74 / 94, 8.8 M 246 / 232, 9.1 M
+//   121 / 116, 18 M 218 / 209, 36 M 449 / 420, 72 M 843 / 817; backward 9.1 M 299 / 294,
+//   18 M 551 / 511, 72 M 2065 / 2022;
+//   float32, two: 10 M 101 / 105, 14 M 147 / 147 (backward 376 / 382), 27 M 309 / 302;
+//   bf16 with rows of 129-256 points (or longer ones unsplit) on the VALU beside the matrix
+//   cores': 1.1 M 40 / 50, 2.2 M 69 / 67, 3.4 M 54 / 54, 4.5 M 86 / 75, 18.6 M 158 / 151.
+// Several launches of the matrix cores alone stay on one stream (the long row's two in dk:
+// backward 1551 / 1553).
 constexpr int64_t kForkDirect = int64_t(1) << 21;
-constexpr int64_t kForkRowPoints = int64_t(1) << 25;
+constexpr int64_t kForkRowsMany = int64_t(1) << 23;
+constexpr int64_t kForkRowsTwo = int64_t(1) << 24;
+constexpr int64_t kForkRowsHalf = int64_t(1) << 21;
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 bool aligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) % kAlign) == 0; }
 
@@ -723,12 +733,16 @@ rubiconv_status_t rubiconv_plan(rubiconv_plan_t* out, int B, int N, int D, int L
     for (const Seg& d : h.direct_docs) direct_tokens += d.len;
     pl->fork_direct = direct_tokens * h.D >= kForkDirect;
     // (most plans have one row launch; the filter gradient's sum groups and long rows are two)
-    int row_launches = (h.doc_task_seg.empty() ? 0 : 1) +
-                       std::max(h.row_all.nblk > 0 ? 1 : 0, (h.row_sum.nblk > 0 ? 1 : 0) + (h.row_own.nblk > 0 ? 1 : 0));
+    int valu_launches = h.doc_task_seg.empty() ? 0 : 1;
     for (const Seg& c : h.classes)
-        if (valu_rows(h, c.m)) ++row_launches;
-    pl->fork_rows = row_launches > 1 &&
-                    (h.grid_points + h.grid_points_lr) * h.npb * kPairsPerBlock >= kForkRowPoints;
+        if (valu_rows(h, c.m)) ++valu_launches;
+    const int row_launches =
+        valu_launches + std::max(h.row_all.nblk > 0 ? 1 : 0, (h.row_sum.nblk > 0 ? 1 : 0) + (h.row_own.nblk > 0 ? 1 : 0));
+    if (row_launches > 1) {
+        const int64_t pts = (h.grid_points + h.grid_points_lr) * h.npb * kPairsPerBlock;
+        pl->fork_rows = h.grid_half ? valu_launches > 0 && pts >= kForkRowsHalf
+                                    : pts >= (row_launches > 2 ? kForkRowsMany : kForkRowsTwo);
+    }
     rubiconv_status_t st = upload(pl, stream);
     if (st != RUBICONV_OK) {
         if (pl->uploaded) {
