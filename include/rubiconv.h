@@ -139,6 +139,9 @@ typedef enum {
  * (read when the plan is made) gives rows of at most 128 points on the matrix cores
  * (bf16 inputs) the smallest integer m_i instead, as Algorithm 1 allows: the same
  * exact result on fewer grid points.
+ * Independent launches run on side streams of the plan where they are large enough for
+ * the fork and join to pay; RUBICONV_FORK = 0 (read when the plan is made) keeps all of
+ * them on the caller's stream and 1 forks them at any size (the same results).
  *   stream          HIP stream the upload of the plan's device tables is enqueued on
  *                   (hipMemcpyAsync from a host copy the plan keeps): work that uses
  *                   the plan on this stream is ordered after it; other streams must
@@ -149,7 +152,7 @@ typedef enum {
  * order with other device work);
  * it does not wait for the upload.
  * Errors: RUBICONV_ERR_ARG (also for a malformed RUBICONV_DIRECT_MAX,
- * RUBICONV_DIRECT_MFMA, RUBICONV_CLASS_MERGE or RUBICONV_PRESCALE),
+ * RUBICONV_DIRECT_MFMA, RUBICONV_CLASS_MERGE, RUBICONV_PRESCALE or RUBICONV_FORK),
  * RUBICONV_ERR_SEQLENS, RUBICONV_ERR_UNSUPPORTED (n1 not supported, a document
  * so long that its row DFT would exceed the largest supported size, or a shape whose
  * kernels would need buffer offsets of 32 bits or more: a document's or size

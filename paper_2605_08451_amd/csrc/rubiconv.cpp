@@ -743,6 +743,15 @@ rubiconv_status_t rubiconv_plan(rubiconv_plan_t* out, int B, int N, int D, int L
         pl->fork_rows = h.grid_half ? valu_launches > 0 && pts >= kForkRowsHalf
                                     : pts >= (row_launches > 2 ? kForkRowsMany : kForkRowsTwo);
     }
+    // RUBICONV_FORK = 0 keeps every launch on the calling stream, 1 forks whatever can be
+    if (const char* v = std::getenv("RUBICONV_FORK")) {
+        if (std::strcmp(v, "0") != 0 && std::strcmp(v, "1") != 0) {
+            delete pl;
+            return RUBICONV_ERR_ARG;
+        }
+        pl->fork_direct = v[0] == '1' && !h.direct_docs.empty();
+        pl->fork_rows = v[0] == '1' && row_launches > 1;
+    }
     rubiconv_status_t st = upload(pl, stream);
     if (st != RUBICONV_OK) {
         if (pl->uploaded) {

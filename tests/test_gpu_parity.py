@@ -448,3 +448,54 @@ def test_filter_transpose_edges(device, D, L):
         W = wl.make_case([[150, 31]], D=D, L=L, x_dtype=dtype, seed=D + L)
         y, _ = run_gpu(W, device)
         assert rel_l2(y, reference(W)) <= bar, (dtype, D, L)
+
+
+@pytest.mark.parametrize("dtype, D", [("f32", 70), ("bf16", 64), ("bf16", 70)])
+def test_forked_launches(device, monkeypatch, dtype, D):
+    """Launches forked to the plan's side streams at any size: direct documents beside row
+    launches of every kind (float32: registers and one per size; bf16: the matrix cores', rows
+    of 129-256 points, long rows), which share a side stream.  Forward, dx, dk and the fused
+    backward, then the calls of two caller streams on one plan in turn, give the bits of the
+    plan that forks nothing."""
+    import torch
+    import paper_2605_08451_amd as rc
+    monkeypatch.setenv("RUBICONV_DIRECT_MAX", "64")
+    rows = [[3, 64, 17, 200, 900, 1500, 2500, 41, 500] + [60] * 5, [20000], [18000, 1, 64]]
+    N = max(map(sum, rows))
+    rows = [r + [N - sum(r)] if sum(r) < N else r for r in rows]
+    W = wl.make_case(rows, D=D, L=N, x_dtype=dtype, seed=D)
+    x, k = to_device(W, device)
+    dy = torch.randn(x.shape, generator=torch.Generator(device).manual_seed(1), device=device).to(x.dtype)
+
+    def make(fork):
+        monkeypatch.setenv("RUBICONV_FORK", fork)
+        plan = rc.Plan(W.cu_seqlens, N=N, D=D, L=N, x_dtype=dtype, y_dtype=dtype)
+        assert plan.info()["n_direct"] > 0
+        return plan, rc.filter_spectrum(plan, k)
+
+    def calls(plan, spec, x, dy, ws, dws):
+        dx, dk = rc.packed_conv_backward(plan, x, dy, spec, workspace=dws)
+        return [rc.packed_conv(plan, x, spec, workspace=ws), rc.packed_conv_dx(plan, dy, spec, workspace=ws),
+                rc.packed_conv_dk(plan, x, dy, workspace=dws), dx, dk]
+
+    def space(plan):
+        return plan.new_workspace(device), plan.new_dk_workspace(device)
+
+    plan0, spec0 = make("0")
+    want = [calls(plan0, spec0, x * s, dy, *space(plan0)) for s in (1, 0.25)]
+    plan, spec = make("1")
+    for a, b in zip(want[0], calls(plan, spec, x, dy, *space(plan))):
+        assert torch.equal(a, b)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    inputs, spaces, got = [x * 1, x * 0.25], [space(plan), space(plan)], [[], []]
+    torch.cuda.synchronize()
+    for _ in range(3):
+        for i, st in enumerate(streams):
+            with torch.cuda.stream(st):
+                got[i].append(calls(plan, spec, inputs[i], dy, *spaces[i]))
+    torch.cuda.synchronize()
+    for i in range(2):
+        for outs in got[i]:
+            for a, b in zip(want[i], outs):
+                assert torch.equal(a, b), i
