@@ -88,6 +88,10 @@ static_assert(sizeof(Seg) % 8 == 0, "Seg must stay 8-byte aligned in arrays");
 struct RowGroup {
     int32_t first, count, n1, nb;
 };
+// Rows of at most kShortRowBlocks blocks take a launch of their own beside longer ones when they
+// hold this many grid points times pairs, by the longest's block count: up to 8, 6, 4
+constexpr int kShortRowBlocks = 2;
+constexpr int64_t kShortRowPoints8 = 7 << 19, kShortRowPoints6 = 1 << 23, kShortRowPoints4 = 7 << 22;
 // Rows of at most this many blocks keep a second set of operands for their partner rows, with
 // the partner's input twiddle folded in: one fp16 rounding less than applying it to the row
 constexpr int kTwinBlocks = 2;

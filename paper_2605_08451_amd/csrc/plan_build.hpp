@@ -53,8 +53,11 @@ struct HostPlan {
     struct RowLaunch { int blk0 = 0, nblk = 0, max_nb = 0; double work = 0; };
     std::vector<int32_t> row_docs;
     std::vector<RowGroup> row_groups;
+    std::vector<int64_t> row_group_points;  // per group: its documents' grid points
     std::vector<int32_t> row_blocks;
-    RowLaunch row_all, row_sum, row_own;  // forward and dx; filter gradient: sum groups, long rows
+    // forward and dx; filter gradient: sum groups, long rows.  Each one launch, or two, the longer
+    // rows first (add_launches)
+    std::vector<RowLaunch> row_all, row_sum, row_own;
     // filter gradient outputs: the documents whose rows hold correlations after the row
     // pass (sum-group leaders and every document outside the sum groups), as copies of
     // their segments with the second rows their own and columns renumbered (dk_segs,

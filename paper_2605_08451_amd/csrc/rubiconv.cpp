@@ -512,7 +512,8 @@ hipError_t enqueue_rows(rubiconv_plan_s* plan, const void* fgrid, int64_t fgrid_
     struct Launch {
         int cls;       // -1: generic kernel; >= 0: register-resident kernel of that class
         double work;
-        const HostPlan::RowLaunch* rows = nullptr;  // the matrix-core launch
+        const HostPlan::RowLaunch* rows = nullptr;  // a matrix-core launch (or the fp32 registers')
+        bool sum = false;                           // of sum groups
     };
     std::vector<Launch> launches;
     if (!h.doc_task_seg.empty()) launches.push_back({-1, 1e30});
@@ -521,23 +522,23 @@ hipError_t enqueue_rows(rubiconv_plan_s* plan, const void* fgrid, int64_t fgrid_
         if (!valu_rows(h, m)) continue;
         launches.push_back({static_cast<int>(c), static_cast<double>(m) * h.classes[c].nlist});
     }
-    for (const HostPlan::RowLaunch* r : {own_rows ? &h.row_sum : &h.row_all, own_rows ? &h.row_own : nullptr})
-        if (r != nullptr && r->nblk > 0) launches.push_back({-1, r->work, r});
-    std::sort(launches.begin(), launches.end(),
+    for (const HostPlan::RowLaunch& r : own_rows ? h.row_sum : h.row_all) launches.push_back({-1, r.work, &r, own_rows});
+    if (own_rows)
+        for (const HostPlan::RowLaunch& r : h.row_own) launches.push_back({-1, r.work, &r});
+    std::stable_sort(launches.begin(), launches.end(),
               [](const Launch& a, const Launch& b) { return a.work > b.work; });
     // the largest launch runs on the calling stream itself, the others on side streams
     const int nside = std::min<int>(rubiconv_plan_s::kSideStreams, static_cast<int>(launches.size()) - 1);
     auto launch_one = [&](const Launch& L, hipStream_t s) -> hipError_t {
         if (L.rows != nullptr) {
-            const bool sum = L.rows == &h.row_sum;
             if (!half)
                 return rubiconv::launch_row_reg(grid, plan->grid_pb_stride, fgrid, fgrid_pb_stride, t.segs,
                                                 plan->row_docs, plan->row_groups,
-                                                plan->row_blocks + 2 * L.rows->blk0, L.rows->nblk, h.npb, corr, s, sum);
+                                                plan->row_blocks + 2 * L.rows->blk0, L.rows->nblk, h.npb, corr, s, L.sum);
             return rubiconv::launch_row_groups(L.rows->max_nb, grid, plan->grid_pb_stride, fgrid, fgrid_pb_stride,
                                                t.segs, plan->row_docs, plan->row_groups,
                                                plan->row_blocks + 2 * L.rows->blk0, L.rows->nblk, plan->dense_tab,
-                                               h.npb, corr, s, sum, sum ? dscale : 1.0f, sum && out2);
+                                               h.npb, corr, s, L.sum, L.sum ? dscale : 1.0f, L.sum && out2);
         }
         if (L.cls < 0)
             return rubiconv::launch_row_conv(h.n1, half, grid, plan->grid_pb_stride, fgrid,
@@ -737,7 +738,7 @@ rubiconv_status_t rubiconv_plan(rubiconv_plan_t* out, int B, int N, int D, int L
     for (const Seg& c : h.classes)
         if (valu_rows(h, c.m)) ++valu_launches;
     const int row_launches =
-        valu_launches + std::max(h.row_all.nblk > 0 ? 1 : 0, (h.row_sum.nblk > 0 ? 1 : 0) + (h.row_own.nblk > 0 ? 1 : 0));
+        valu_launches + static_cast<int>(std::max(h.row_all.size(), h.row_sum.size() + h.row_own.size()));
     if (row_launches > 1) {
         const int64_t pts = (h.grid_points + h.grid_points_lr) * h.npb * kPairsPerBlock;
         pl->fork_rows = h.grid_half ? valu_launches > 0 && pts >= kForkRowsHalf

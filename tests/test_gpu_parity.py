@@ -499,3 +499,39 @@ def test_forked_launches(device, monkeypatch, dtype, D):
         for outs in got[i]:
             for a, b in zip(want[i], outs):
                 assert torch.equal(a, b), i
+
+
+def test_short_rows_beside_long_ones(device, monkeypatch):
+    """Short rows that hold enough of the grid beside a document of 8 blocks take a launch of
+    their own: batched rows, rows of one and of two blocks, class sums of several documents and
+    of one.  Forward, dx, dk and the fused backward against the oracle, 5e-3 per document
+    (twice the fp16 grids' and the bf16 output's 2e-3)."""
+    import torch
+    import paper_2605_08451_amd as rc
+    import tests.test_gpu_grad as tg
+    monkeypatch.setenv("RUBICONV_DIRECT_MAX", "0")
+    rng = np.random.default_rng(41)
+    rows = []
+    for first in ([30000], [7000, 4100]):
+        r = list(first)
+        while sum(r) < 42000:
+            r.append(int(rng.choice([rng.integers(100, 2000), rng.integers(2100, 8000)], p=[0.8, 0.2])))
+        rows.append(r + [45000 - sum(r)] if sum(r) < 45000 else r[:-1] + [45000 - sum(r[:-1])])
+    W = wl.make_case(rows, D=128, L=64, x_dtype="bf16", seed=41)
+    plan = rc.Plan(W.cu_seqlens, N=W.N, D=W.D, L=64, x_dtype="bf16")
+    m = plan.doc_table()[:, 4]
+    short = m <= 32
+    assert m.max() > 96 and m[short].sum() * 256 * 64 >= 7 << 19 and (m <= 8).any() and (m > 16)[short].any()
+    y, _ = run_gpu(W, device)
+    g, d = assert_parity(y, reference(W), W.cu_seqlens, "bf16", "short beside long")
+    assert d <= 5e-3, d
+    dyv, dx, dk, _ = tg._run(W, device, seed=42)
+    g, d = assert_parity(dx, oracle.grad_x(W.filters, dyv, W.cu_seqlens), W.cu_seqlens, "bf16", "dx")
+    assert d <= 5e-3, d
+    refk = oracle.grad_k(W.x, dyv, W.cu_seqlens, W.L)
+    assert rel_l2(dk, refk) <= 5e-3
+    x, k = to_device(W, device)
+    dy = torch.from_numpy(dyv.astype(np.float32)).to(torch.bfloat16).to(device)
+    dxf, dkf = rc.packed_conv_backward(plan, x, dy, rc.filter_spectrum(plan, k))
+    np.testing.assert_array_equal(dxf.float().cpu().numpy(), dx.astype(np.float32))
+    assert rel_l2(dkf.cpu().numpy().astype(np.float64), refk) <= 5e-3
