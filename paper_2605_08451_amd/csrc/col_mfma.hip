@@ -563,9 +563,10 @@ hipError_t launch_col_fwd_mfma(int src_dtype, const void* src, int64_t src_row_s
         return hipErrorInvalidValue;
     const int ntasks = n_cols * npb;
     // the redo launch mostly does nothing: 512 workgroups (two per CU) that loop over the
-    // tasks start and leave faster than one workgroup per four tasks (and than 1024, 1 us
-    // slower), and a real redo at two workgroups per CU runs a tenth longer than at four.  Its
-    // magnitudes are those of the first launch, one per workgroup of that launch (wgs)
+    // tasks.  Measured, us of a call whose guess held / of what a redo adds, at 512, 1024 and one
+    // workgroup per four tasks: mid-length 368, 369, 372 / 122, 124, 106; LM packing 142, 142,
+    // 144 / 23, 17, 20; long row 602, 602, 606 / 132, 137, 118.  (512 of eight waves: 120, 22,
+    // 137.)  Its magnitudes are those of the first launch, one per workgroup of that launch (wgs)
     const int wgs = (ntasks + 3) / 4;
     const dim3 g(amax_in != nullptr ? std::min(wgs, 512) : wgs), b(256);
     const u4* mt = static_cast<const u4*>(mtab);
