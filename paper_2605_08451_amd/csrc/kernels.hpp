@@ -14,9 +14,11 @@
 // grid point of (u, j) in a segment = grid_off + u * m + j.
 // The filter "spectrum" is the filter pairs' class grids after the column stage,
 // same layout, class grid point of (u, j) = spec_off + u * m + j.  The stored
-// grids are the DFTs scaled by 1 / sqrt(N1) (folded into the w_P^r table); the
-// row pass scales the filter spectra by sqrt(N1) / (2 m), so that
-// 1/sqrt(N1) * 1/m * 1/sqrt(N1) = 1/P overall and fp16 values stay O(|x|).
+// grids are the DFTs scaled by 1 / sqrt(N1) (folded into the w_P^r table), the documents'
+// times a power of two (Seg::in_scale); a row pass leaves W / m times sqrt(N1), so that with the
+// inverse column pass's 1 / sqrt(N1) the result is 1 / P overall and fp16 values stay O(|x|): the
+// VALU kernels scale the filter spectra by sqrt(N1) / (2 m), the matrix-core ones split it
+// between their operands and their inverse (row_dense.hip).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -80,8 +82,9 @@ hipError_t launch_row_conv(int n1, bool half, void* grid, int64_t grid_pb_stride
                            const void* fgrid, int64_t fgrid_pb_stride, const LaunchTables& t,
                            int n_tasks, int npb, int lds_bytes, int corr, hipStream_t stream);
 
-// Register-resident row pass for a listed row size m (row_sizes.hpp) over the
-// nlist documents list[0..nlist) of that size.
+// VALU row pass for a listed row size m (row_sizes.hpp) over the nlist documents
+// list[0..nlist) of that size: m > kMaxRegM on complex fp32 grids, m > 16 * kMaxDenseBlocks on
+// complex fp16 ones (hipErrorInvalidValue otherwise).
 hipError_t launch_row_fast(int m, bool half, void* grid, int64_t grid_pb_stride, const void* fgrid,
                            int64_t fgrid_pb_stride, const Seg* segs, const int32_t* list,
                            int nlist, const float2* tw, int n1, int npb, int corr,

@@ -1,4 +1,6 @@
-// row_fast.hip -- register-resident row pass for row sizes m = M1 * M2 <= 256.
+// row_fast.hip -- row passes on the VALU for rows of at most 256 points: row_fast_kernel for
+// m = M1 * M2 (complex fp32 grids from 9 points on, complex fp16 grids from 129 on, where the
+// matrix cores' rows end), and row_reg_kernel below for shorter fp32 rows.
 //
 // One workgroup handles grid row u (0 <= u <= N1/2) of one document and its
 // conjugate partner row (N1 - u) mod N1, for the 16 channel pairs of one pair
@@ -288,10 +290,15 @@ hipError_t launch_row_fast(int m, bool half, void* grid, int64_t grid_pb_stride,
     switch (m) {
 #define RUBICONV_CASE(mm, a, b)                                                                  \
     case mm:                                                                                     \
-        return half ? launch_mg<a, b, __half2>(grid, grid_pb_stride, fgrid, fgrid_pb_stride, segs, \
-                                               list, nlist, tw, n1, npb, corr, stream)            \
-                    : launch_mg<a, b, float2>(grid, grid_pb_stride, fgrid, fgrid_pb_stride, segs,  \
-                                              list, nlist, tw, n1, npb, corr, stream);
+        if constexpr ((mm) > 16 * kMaxDenseBlocks)                                               \
+            if (half)                                                                            \
+                return launch_mg<a, b, __half2>(grid, grid_pb_stride, fgrid, fgrid_pb_stride, segs, list, nlist, tw, \
+                                                n1, npb, corr, stream);                          \
+        if constexpr ((mm) > kMaxRegM)                                                           \
+            if (!half)                                                                           \
+                return launch_mg<a, b, float2>(grid, grid_pb_stride, fgrid, fgrid_pb_stride, segs, list, nlist, tw, \
+                                               n1, npb, corr, stream);                           \
+        return hipErrorInvalidValue;
         RUBICONV_ROW_SIZES(RUBICONV_CASE)
 #undef RUBICONV_CASE
         default:
