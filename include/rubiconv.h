@@ -292,7 +292,7 @@ size_t rubiconv_dk_workspace_bytes(rubiconv_plan_t plan);
  *              aligned; dk must not overlap it.
  *   stream     HIP stream the work is enqueued on.
  * The sums over documents run in a fixed order (within a size class's group, then over
- * the groups' and other documents' correlations, longest first, from 32 of them on in
+ * the groups' and other documents' correlations, longest first, with many documents in
  * chunks of 16 first, ties in
  * table order), so results are deterministic.
  * Errors: RUBICONV_ERR_ARG, RUBICONV_ERR_UNSUPPORTED (a plan of 2^31 grid points

@@ -721,12 +721,11 @@ __global__ __launch_bounds__(256) void direct_kernel(const TA* __restrict__ a, c
 // dk[D][L].  A workgroup owns 8 lags x 64 VEC channels; its four waves split the
 // documents (rounds of four documents, round k to wave k mod 4) and their partial
 // sums are added in wave order through LDS, so the order of every sum is fixed.
-// segs lists the documents longest first: a wave stops at the first round whose
+// The documents are listed longest first (LagDocs): a wave stops at the first round whose
 // longest document ends before the workgroup's lags.  Lanes run along channels for
 // the reads (VEC channels per lane) and along lags for the writes.
 template <int VEC>
-__global__ __launch_bounds__(256) void lag_sum_kernel(const float* __restrict__ r,
-                                                      const Seg* __restrict__ segs, int n_docs,
+__global__ __launch_bounds__(256) void lag_sum_kernel(const float* __restrict__ r, LagDocs docs,
                                                       int N, int D, int L, float* __restrict__ dk) {
     typedef float fv __attribute__((ext_vector_type(VEC)));
     constexpr int C = 64 * VEC;                 // channels per workgroup
@@ -739,6 +738,8 @@ __global__ __launch_bounds__(256) void lag_sum_kernel(const float* __restrict__ 
     const int tile = 4 * (8 * (b >> 5) + (b & 7)) + ((b >> 3) & 3);
     const int tau0 = tile * T, d0 = blockIdx.y * C;
     if (tau0 >= L) return;  // grid padding; no barrier has been reached
+    const Seg* segs = tau0 < docs.lead_lags ? docs.lead : docs.segs;
+    const int n_docs = tau0 < docs.lead_lags ? docs.n_lead : docs.n;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int d = d0 + VEC * lane;
     fv acc[T];
@@ -788,8 +789,7 @@ __global__ __launch_bounds__(256) void lag_sum_kernel(const float* __restrict__ 
 // most of those waves would idle): each wave owns 8 lags of the workgroup's 32 and sums
 // every document itself, longest first, in document order; the workgroup's 32 x 256
 // block of dk goes out through LDS with lanes along lags (128-byte runs per channel).
-__global__ __launch_bounds__(256) void lag_sum_few_kernel(const float* __restrict__ r,
-                                                         const Seg* __restrict__ segs, int n_docs,
+__global__ __launch_bounds__(256) void lag_sum_few_kernel(const float* __restrict__ r, LagDocs docs,
                                                          int N, int D, int L, float* __restrict__ dk) {
     constexpr int C = 256;  // channels per workgroup, four per lane
     constexpr int T = 8;    // lags per wave
@@ -797,6 +797,8 @@ __global__ __launch_bounds__(256) void lag_sum_few_kernel(const float* __restric
     __shared__ float part[4 * T][C + 1];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int tau0 = blockIdx.x * (4 * T) + w * T, d0 = blockIdx.y * C;
+    const Seg* segs = tau0 < docs.lead_lags ? docs.lead : docs.segs;
+    const int n_docs = tau0 < docs.lead_lags ? docs.n_lead : docs.n;
     const int d = d0 + 4 * lane;
     float4 acc[T];
 #pragma unroll
@@ -849,7 +851,8 @@ __global__ __launch_bounds__(256) void lag_sum_few_kernel(const float* __restric
 // document order, onto the first one's.  The last step then sums the chunks' first documents
 // only: with hundreds of short documents it would leave the few workgroups of the low lags
 // nearly all the reading (stress workload, 320 documents, 282 of at most 64 tokens: 90 us
-// for the one step, 19 + 19 for the two).  A value is read and written by one thread alone.
+// for the one step, 19 + 19 for the two).  Where the line lies is in plan_build.cpp.  A value is
+// read and written by one thread alone.
 template <int VEC>
 __global__ __launch_bounds__(256) void lag_chunk_kernel(float* __restrict__ r, const Seg* __restrict__ segs,
                                                         const int2* __restrict__ blocks, int n_docs, int N, int D,
@@ -1137,20 +1140,21 @@ hipError_t launch_lag_chunks(float* r, const Seg* segs, const int32_t* blocks, i
     return hipGetLastError();
 }
 
-hipError_t launch_lag_sum(const float* r, const Seg* segs, int n_docs, int N, int D, int L,
-                          float* dk, hipStream_t stream) {
+hipError_t launch_lag_sum(const float* r, const LagDocs& docs, int N, int D, int L, float* dk, hipStream_t stream) {
     if (D <= 0 || L <= 0) return hipSuccess;
-    if (D % 4 == 0 && n_docs < 16) {  // fewer documents than the waves' rounds below
+    // fewer documents at any lag than the waves' rounds of the general kernel
+    const bool few = (docs.lead_lags > 0 ? std::max(docs.n_lead, docs.n_past) : docs.n) < 16;
+    if (D % 4 == 0 && few) {
         const dim3 g((L + 31) / 32, (D + 255) / 256), b(256);
-        hipLaunchKernelGGL(lag_sum_few_kernel, g, b, 0, stream, r, segs, n_docs, N, D, L, dk);
+        hipLaunchKernelGGL(lag_sum_few_kernel, g, b, 0, stream, r, docs, N, D, L, dk);
         return hipGetLastError();
     }
     if (D % 4 == 0) {  // whole float4 groups: 16-byte loads (r is 256-byte aligned)
         const dim3 g((L + 255) / 256 * 32, (D + 255) / 256), b(256);
-        hipLaunchKernelGGL(lag_sum_kernel<4>, g, b, 0, stream, r, segs, n_docs, N, D, L, dk);
+        hipLaunchKernelGGL(lag_sum_kernel<4>, g, b, 0, stream, r, docs, N, D, L, dk);
     } else {
         const dim3 g((L + 255) / 256 * 32, (D + 63) / 64), b(256);
-        hipLaunchKernelGGL(lag_sum_kernel<1>, g, b, 0, stream, r, segs, n_docs, N, D, L, dk);
+        hipLaunchKernelGGL(lag_sum_kernel<1>, g, b, 0, stream, r, docs, N, D, L, dk);
     }
     return hipGetLastError();
 }

@@ -187,15 +187,23 @@ hipError_t launch_direct(int mode, int max_len, int a_dtype, const void* a, int 
                          const void* b, const float* taps, const Seg* docs, int n_docs, int N, int D,
                          int L, int out_dtype, void* out, hipStream_t stream);
 
-// dk[d][tau] = sum over documents k < n_docs with tau < min(len_k, L) of
-// r[row_k][start_k + tau][d] (r fp32 [B][N][D]); dk [D][L] fp32, fully written.
-// segs must list the documents by non-increasing length.
-hipError_t launch_lag_sum(const float* r, const Seg* segs, int n_docs, int N, int D, int L,
-                          float* dk, hipStream_t stream);
+// The documents of the filter gradient's last sum, by non-increasing length: all n of them, and
+// for the lags below lead_lags (a multiple of 32; 0: none) the n_lead that hold the others'
+// correlations too (launch_lag_chunks); n_past of the n have lags from lead_lags on.
+struct LagDocs {
+    const Seg* segs = nullptr;
+    int n = 0;
+    const Seg* lead = nullptr;
+    int n_lead = 0, lead_lags = 0, n_past = 0;
+};
 
-// The same sum's first step where documents are many (kLagChunkMin): blocks, (chunk, tile)
+// dk[d][tau] = sum over the documents k with tau < min(len_k, L) of
+// r[row_k][start_k + tau][d] (r fp32 [B][N][D]); dk [D][L] fp32, fully written.
+hipError_t launch_lag_sum(const float* r, const LagDocs& docs, int N, int D, int L, float* dk, hipStream_t stream);
+
+// The same sum's first step at the lags that many documents have: blocks, (chunk, tile)
 // pairs, add each chunk's kLagChunk documents at 4 lags onto the chunk's first document (in
-// place in r); launch_lag_sum then takes the chunks' first documents.
+// place in r).
 hipError_t launch_lag_chunks(float* r, const Seg* segs, const int32_t* blocks, int nblocks, int n_docs, int N, int D,
                              int L, hipStream_t stream);
 

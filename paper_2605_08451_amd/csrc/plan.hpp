@@ -8,6 +8,7 @@
 // per-row-task table.
 #pragma once
 
+#include <cstddef>
 #include <cstdint>
 
 namespace rubiconv {
@@ -43,10 +44,9 @@ constexpr int kMaxGroupDocs = 4;
 // matrix-core row pass adds before its one inverse transform (fp16 sums: the bound on
 // one document's product leaves room for far more)
 constexpr int kMaxSumDocs = 8;
-// Filter gradient's last sum: with at least kLagChunkMin documents it first adds chunks of
-// kLagChunk documents each
+// Filter gradient's last sum: with many documents it first adds chunks of kLagChunk each
 constexpr int kLagChunk = 16;
-constexpr int kLagChunkMin = 32;
+constexpr size_t kLagChunkMin = 32, kLagChunkMany = 96;
 // Rows of at most this many points are batched 16 / m to a matrix-core block, when
 // they hold at least 1 / kBatchMinShare of the grid (measured: a step of mostly 5-8-point
 // rows 168 -> 160 us; 1% slower when a few such documents sit among long ones, whose

@@ -67,9 +67,11 @@ struct HostPlan {
     std::vector<int32_t> dk_col_seg;
     std::vector<Seg> dk_sum_segs;
     // with many of them: the first step's workgroups, (chunk, 4-lag tile) pairs over
-    // dk_sum_segs, and the chunks' first documents, longest first
+    // dk_sum_segs, and the chunks' first documents, longest first, which stand for all below
+    // lead_lags; lag_past documents have lags from there on
     std::vector<int32_t> lag_blocks;
     std::vector<Seg> lag_lead;
+    int lead_lags = 0, lag_past = 0;
     // long rows: the documents' and classes' first-level items, and the virtual documents
     // (m = m2, offsets into the sub-row regions; spec_off of lr_segs points at the
     // class's sub-rows, of lr_gsegs at the document's own)

@@ -206,7 +206,7 @@ rubiconv_status_t upload(rubiconv_plan_s* pl, hipStream_t stream) {
     }
     if (!h.dk_sum_segs.empty())
         std::memcpy(img.data() + o_ksum, h.dk_sum_segs.data(), h.dk_sum_segs.size() * sizeof(Seg));
-    if (!h.lag_blocks.empty()) {
+    if (!h.lag_lead.empty()) {
         std::memcpy(img.data() + o_lb, h.lag_blocks.data(), h.lag_blocks.size() * 4);
         std::memcpy(img.data() + o_ll, h.lag_lead.data(), h.lag_lead.size() * sizeof(Seg));
     }
@@ -617,12 +617,11 @@ hipError_t enqueue_conv(rubiconv_plan_s* plan, const void* in, int in_dtype, con
 hipError_t enqueue_lag_sum(rubiconv_plan_s* plan, float* r, float* dk, hipStream_t stream) {
     const HostPlan& h = plan->h;
     const int n = static_cast<int>(h.dk_sum_segs.size());
-    if (h.lag_lead.empty())
-        return rubiconv::launch_lag_sum(r, plan->dk_sum_segs, n, h.N, h.D, h.L, dk, stream);
+    const rubiconv::LagDocs docs{plan->dk_sum_segs, n, plan->lag_lead, static_cast<int>(h.lag_lead.size()),
+                                 h.lead_lags, h.lag_past};
     hipError_t e = rubiconv::launch_lag_chunks(r, plan->dk_sum_segs, plan->lag_blocks,
                                                static_cast<int>(h.lag_blocks.size() / 2), n, h.N, h.D, h.L, stream);
-    if (e == hipSuccess)
-        e = rubiconv::launch_lag_sum(r, plan->lag_lead, static_cast<int>(h.lag_lead.size()), h.N, h.D, h.L, dk, stream);
+    if (e == hipSuccess) e = rubiconv::launch_lag_sum(r, docs, h.N, h.D, h.L, dk, stream);
     return e;
 }
 

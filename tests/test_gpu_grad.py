@@ -477,3 +477,21 @@ def test_float_class_sums_keep_lags_apart(device, monkeypatch, m):
     bad = rc.packed_conv_dk(plan, torch.from_numpy(x).to(device), dy.to(device)).cpu().numpy()
     assert np.isnan(bad[:, :n2 - 3]).any(axis=0).all()
     np.testing.assert_array_equal(bad[:, n2:], dk[:, n2:].astype(np.float32))
+
+
+@pytest.mark.parametrize("D", [6, 7, 8])
+def test_lag_sum_low_lags(device, D):
+    """The filter gradient over some 110 documents: with channels in no groups of 4 the chunks
+    are added at the lags that more than 15 documents have, and the longer ones' further lags
+    come straight from them; around that line (documents of 31 to 33 lags and of 95 to 97), one
+    far longer document, filters shorter than it.  Bar 2e-6 as for the other float32 sums."""
+    for cut in (32, 96):
+        lens = [cut - 1, cut, cut + 1] * 5 + [1, 2, 3, 5, 20] * 19 + [700, 300]
+        for L in (cut, 500):
+            W = wl.make_case([lens, [sum(lens)]], D=D, L=L, x_dtype="f32", seed=D + L)
+            dyv, _, dk, _ = _run(W, device, seed=D + 1)
+            ref = oracle.grad_k(W.x, dyv, W.cu_seqlens, L, threads=ORACLE_THREADS)
+            assert rel_l2(dk, ref) <= 2e-6, (D, L, cut, rel_l2(dk, ref))
+            for part in (slice(0, 32), slice(32, 96), slice(96, None)):
+                if np.any(ref[:, part]):
+                    assert rel_l2(dk[:, part], ref[:, part]) <= 4e-6, (D, L, cut, part)
