@@ -106,15 +106,17 @@ constexpr size_t kAlign = 256;
 // against one stream: 0.2 M 54 against 36 us, 4.2 M 177 against 191, 8 M 158 against 171).
 // The row stage's launches, where it has several, by its grid points times pairs (measured,
 // us per convolution, one stream / forked):
-//   float32, three and more (a launch per size class): 4.7 M 74 / 94, 8.8 M 246 / 232, 9.1 M
-//   121 / 116, 18 M 218 / 209, 36 M 449 / 420, 72 M 843 / 817; backward 9.1 M 299 / 294,
-//   18 M 551 / 511, 72 M 2065 / 2022;
+//   float32, seven and more (a launch per size class): 4.1 M 89 / 105, 6.0 M 109 / 99, 6.6 M
+//   122 / 126, 8.0 M 138 / 124, 18 M 218 / 209, 72 M 843 / 817; backward 4.1 M 208 / 226, 6.0 M
+//   243 / 210, 6.6 M 274 / 259, 8.0 M 329 / 309, 18 M 551 / 511, 72 M 2065 / 2022;
+//   three to six: 4.7 M 74 / 94, 6.9 M 75 / 78, 8.3 M 91 / 88, 8.8 M 246 / 232, 14.6 M 166 / 160;
 //   float32, two: 10 M 101 / 105, 14 M 147 / 147 (backward 376 / 382), 27 M 309 / 302;
 //   bf16 with rows of 129-256 points (or longer ones unsplit) on the VALU beside the matrix
 //   cores': 1.1 M 40 / 50, 2.2 M 69 / 67, 3.4 M 54 / 54, 4.5 M 86 / 75, 18.6 M 158 / 151.
 // Several launches of the matrix cores alone stay on one stream (the long row's two in dk:
 // backward 1551 / 1553).
 constexpr int64_t kForkDirect = int64_t(1) << 21;
+constexpr int64_t kForkRowsMost = int64_t(11) << 19;
 constexpr int64_t kForkRowsMany = int64_t(1) << 23;
 constexpr int64_t kForkRowsTwo = int64_t(1) << 24;
 constexpr int64_t kForkRowsHalf = int64_t(1) << 21;
@@ -741,7 +743,9 @@ rubiconv_status_t rubiconv_plan(rubiconv_plan_t* out, int B, int N, int D, int L
     if (row_launches > 1) {
         const int64_t pts = (h.grid_points + h.grid_points_lr) * h.npb * kPairsPerBlock;
         pl->fork_rows = h.grid_half ? valu_launches > 0 && pts >= kForkRowsHalf
-                                    : pts >= (row_launches > 2 ? kForkRowsMany : kForkRowsTwo);
+                                    : pts >= (row_launches > 6   ? kForkRowsMost
+                                              : row_launches > 2 ? kForkRowsMany
+                                                                 : kForkRowsTwo);
     }
     // RUBICONV_FORK = 0 keeps every launch on the calling stream, 1 forks whatever can be
     if (const char* v = std::getenv("RUBICONV_FORK")) {
