@@ -104,21 +104,22 @@ constexpr size_t kAlign = 256;
 // 20 us with nothing running, so launches go to side streams only where they are long enough
 // to fill that.  The direct path from kForkDirect token-channels on (measured per step, fork
 // against one stream: 0.2 M 54 against 36 us, 4.2 M 177 against 191, 8 M 158 against 171).
-// The row stage's launches, where it has several, by its grid points times pairs (measured,
-// us per convolution, one stream / forked):
-//   float32, seven and more (a launch per size class): 4.1 M 89 / 105, 6.0 M 109 / 99, 6.6 M
-//   122 / 126, 8.0 M 138 / 124, 18 M 218 / 209, 72 M 843 / 817; backward 4.1 M 208 / 226, 6.0 M
-//   243 / 210, 6.6 M 274 / 259, 8.0 M 329 / 309, 18 M 551 / 511, 72 M 2065 / 2022;
-//   three to six: 4.7 M 74 / 94, 6.9 M 75 / 78, 8.3 M 91 / 88, 8.8 M 246 / 232, 14.6 M 166 / 160;
-//   float32, two: 10 M 101 / 105, 14 M 147 / 147 (backward 376 / 382), 27 M 309 / 302;
-//   bf16 with rows of 129-256 points (or longer ones unsplit) on the VALU beside the matrix
-//   cores': 1.1 M 40 / 50, 2.2 M 69 / 67, 3.4 M 54 / 54, 4.5 M 86 / 75, 18.6 M 158 / 151.
-// Several launches of the matrix cores alone stay on one stream (the long row's two in dk:
-// backward 1551 / 1553).
+// The row stage's launches, where it has several:
+//   float32 (rows in registers, one launch per larger size, the generic kernel): by what the
+//   launches but the largest would take one after the other, in grid points times pairs, each
+//   launch counting kForkRowLatency per point of its rows besides, as a few documents of long
+//   rows do not fill the chip (measured by that count, one stream / forked, us: 2.7 M 75 / 84,
+//   4.5 M 74 / 94, 5.3 M 100 / 100, 5.4 M 147 / 147 with a backward of 376 / 382, 6.2 M 92 /
+//   106 and 216 / 211, 7.5 M 109 / 99 and 243 / 210, 7.8 M 120 / 123 and 280 / 266, 8.1 M 191 /
+//   166, 9.9 M 195 / 185 and 505 / 488, 12.7 M 162 / 156 and 418 / 404, 33 M 553 / 501); beside
+//   the generic kernel, which outlasts the others, from less (4.2 M 246 / 232 and 575 / 547);
+//   bf16: where rows of 129-256 points (or longer ones unsplit) run on the VALU beside the
+//   matrix cores', by all grid points times pairs: 1.1 M 40 / 50, 2.2 M 69 / 67, 3.4 M 54 / 54,
+//   4.5 M 86 / 75, 18.6 M 158 / 151.  Several launches of the matrix cores alone stay on one
+//   stream (the long row's two in dk: backward 1551 / 1553).
 constexpr int64_t kForkDirect = int64_t(1) << 21;
-constexpr int64_t kForkRowsMost = int64_t(11) << 19;
-constexpr int64_t kForkRowsMany = int64_t(1) << 23;
-constexpr int64_t kForkRowsTwo = int64_t(1) << 24;
+constexpr int64_t kForkRowLatency = 10000;
+constexpr int64_t kForkRows = 7000000, kForkRowsGeneric = 4000000;
 constexpr int64_t kForkRowsHalf = int64_t(1) << 21;
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 bool aligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) % kAlign) == 0; }
@@ -740,12 +741,30 @@ rubiconv_status_t rubiconv_plan(rubiconv_plan_t* out, int B, int N, int D, int L
         if (valu_rows(h, c.m)) ++valu_launches;
     const int row_launches =
         valu_launches + static_cast<int>(std::max(h.row_all.size(), h.row_sum.size() + h.row_own.size()));
-    if (row_launches > 1) {
+    if (row_launches > 1 && h.grid_half) {
         const int64_t pts = (h.grid_points + h.grid_points_lr) * h.npb * kPairsPerBlock;
-        pl->fork_rows = h.grid_half ? valu_launches > 0 && pts >= kForkRowsHalf
-                                    : pts >= (row_launches > 6   ? kForkRowsMost
-                                              : row_launches > 2 ? kForkRowsMany
-                                                                 : kForkRowsTwo);
+        pl->fork_rows = valu_launches > 0 && pts >= kForkRowsHalf;
+    } else if (row_launches > 1) {
+        struct { int64_t pts = 0; int m = 0; } reg, generic;
+        int64_t all = 0, largest = 0, largest_cost = 0;  // of the launches
+        auto count = [&](int64_t pts, int m) {
+            const int64_t cost = pts + kForkRowLatency * m;
+            all += cost;
+            if (pts > largest) largest = pts, largest_cost = cost;
+        };
+        for (const Seg& c : h.classes) {
+            const int64_t pts = int64_t(c.P) * c.nlist * h.npb * kPairsPerBlock;
+            if (valu_rows(h, c.m)) {
+                count(pts, c.m);
+            } else {
+                auto& one = c.m <= rubiconv::kMaxRegM ? reg : generic;
+                one.pts += pts;
+                one.m = std::max(one.m, static_cast<int>(c.m));
+            }
+        }
+        count(reg.pts, reg.m);
+        count(generic.pts, generic.m);
+        pl->fork_rows = all - largest_cost >= (generic.pts > 0 ? kForkRowsGeneric : kForkRows);
     }
     // RUBICONV_FORK = 0 keeps every launch on the calling stream, 1 forks whatever can be
     if (const char* v = std::getenv("RUBICONV_FORK")) {
