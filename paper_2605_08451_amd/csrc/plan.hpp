@@ -40,9 +40,9 @@ constexpr int kDocPointCost = 10;
 constexpr int kClassPointCost = 3;
 // Documents of one size class that share a row task of the matrix-core row pass
 constexpr int kMaxGroupDocs = 4;
-// Filter gradient: documents of one size class whose correlation products the
-// matrix-core row pass adds before its one inverse transform (fp16 sums: the bound on
-// one document's product leaves room for far more)
+// Filter gradient: documents of one size class whose correlation products the matrix-core row
+// pass adds before its one inverse transform.  The sums are fp16: eight documents' 4 W may reach
+// 2^14 of its 2^16 (row_gain in plan_build.cpp), so 16 would still fit and 32 not
 constexpr int kMaxSumDocs = 8;
 // Filter gradient's last sum: with many documents it first adds chunks of kLagChunk each
 constexpr int kLagChunk = 16;

@@ -227,19 +227,22 @@ def test_long_row_sizes_precision(device, n1, monkeypatch):
         assert d <= 5e-3, (n1, L, d)
 
 
-@pytest.mark.parametrize("family", ["lds", "batch", "partner"])
+@pytest.mark.parametrize("family", ["twin", "batch", "twiddled4", "twiddled6", "twiddled8"])
 def test_row_kernel_sizes_precision(device, family, monkeypatch):
-    """The same tight bar (5e-3 per document) for the other matrix-core row kernels on the
-    matrix-core column path (D = 32): rows of 2..32 points (row_lds_kernel), rows of at
-    most 8 points batched 16 / m documents to a block (row_batch_kernel) and rows of
-    33..128 points (row_partner_kernel), every size as its own class: 2^a 3^b 5^c sizes
-    and, with rows at their own sizes (RUBICONV_EXACT_ROWS = 1), the others (primes among
-    them), which these kernels take as they are."""
+    """The same tight bar (5e-3 per document, forward and dx) for the matrix-core row kernels on
+    the matrix-core column path (D = 32): rows of 2..32 points (a twin operand set for the
+    partner row), rows of at most 8 points batched 16 / m documents to a block and rows of
+    33..64, 33..96 and 33..128 points (the partner row twiddled), whose launches are those of
+    up to 2, 2, 4, 6 and 8 blocks; every size as its own class: 2^a 3^b 5^c sizes and, with
+    rows at their own sizes (RUBICONV_EXACT_ROWS = 1), the others (primes among them), which
+    these kernels take as they are.  dk (the summing launches of the same block counts) globally,
+    5e-3 too (about 1e-3 measured)."""
+    import tests.test_gpu_grad as tg
     monkeypatch.setenv("RUBICONV_DIRECT_MAX", "0")   # every document on the transform path
     monkeypatch.setenv("RUBICONV_CLASS_MERGE", "0")
     monkeypatch.setenv("RUBICONV_EXACT_ROWS", "1")
     n1 = 256
-    if family == "lds":
+    if family == "twin":
         ks = (2, 3, 4, 5, 6, 8, 9, 10, 12, 15, 16, 18, 20, 24, 25, 27, 30, 32,
               7, 11, 13, 14, 17, 19, 21, 22, 23, 26, 28, 29, 31)
         monkeypatch.setenv("RUBICONV_ROW_BATCH", "0")
@@ -249,6 +252,7 @@ def test_row_kernel_sizes_precision(device, family, monkeypatch):
     else:
         ks = (36, 40, 45, 48, 50, 54, 60, 64, 72, 75, 80, 81, 90, 96, 100, 108, 120, 128,
               33, 37, 41, 44, 47, 53, 59, 61, 67, 71, 77, 83, 89, 97, 101, 109, 113, 127)
+        ks = tuple(k for k in ks if k <= 16 * int(family[-1]))
     # a 7-tap filter: P >= len + 6, so a document of n1 (k - 1) + 3 tokens takes m = k
     lens = [n1 * (k - 1) + 3 if k > 1 else 100 + 7 * i for i, k in enumerate(ks)]
     N = max(lens) + 1
@@ -258,8 +262,14 @@ def test_row_kernel_sizes_precision(device, family, monkeypatch):
     ms = sorted(set(int(m) for m in plan.doc_table()[:, 4]))
     assert all(k in ms for k in ks), (ks, ms)
     g, d = assert_parity(y, reference(W, "fft"), W.cu_seqlens, "bf16", family)
-    print(f"[row kernels] {family}: global {g:.2e}, worst document {d:.2e}", file=sys.stderr, flush=True)
     assert d <= 5e-3, (family, d)
+    dyv, dx, dk, _ = tg._run(W, device, seed=len(ks) + 1)
+    _, dd = assert_parity(dx, oracle.grad_x(W.filters, dyv, W.cu_seqlens), W.cu_seqlens, "bf16", f"dx {family}")
+    assert dd <= 5e-3, (family, dd)
+    gk = rel_l2(dk, oracle.grad_k(W.x, dyv, W.cu_seqlens, W.L))
+    assert gk <= 5e-3, (family, gk)
+    print(f"[row kernels] {family}: global {g:.2e}, worst document {d:.2e}, dx {dd:.2e}, dk {gk:.2e}",
+          file=sys.stderr, flush=True)
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
