@@ -797,8 +797,11 @@ __global__ __launch_bounds__(256) void lag_sum_few_kernel(const float* __restric
     __shared__ float part[4 * T][C + 1];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int tau0 = blockIdx.x * (4 * T) + w * T, d0 = blockIdx.y * C;
-    const Seg* segs = tau0 < docs.lead_lags ? docs.lead : docs.segs;
-    const int n_docs = tau0 < docs.lead_lags ? docs.n_lead : docs.n;
+    // by the workgroup's first lag (the same for all of it, as lead_lags is a multiple of 32): the
+    // segment pointer stays in scalar registers
+    const bool low = static_cast<int>(blockIdx.x) * (4 * T) < docs.lead_lags;
+    const Seg* segs = low ? docs.lead : docs.segs;
+    const int n_docs = low ? docs.n_lead : docs.n;
     const int d = d0 + 4 * lane;
     float4 acc[T];
 #pragma unroll
