@@ -507,11 +507,11 @@ hipError_t enqueue_rows(rubiconv_plan_s* plan, const void* fgrid, int64_t fgrid_
     const HostPlan& h = plan->h;
     const bool half = h.grid_half;
     hipError_t e = hipSuccess;
-    // row pass: one launch for every row the matrix cores take, or of fp32 grids every row
-    // that fits a thread's registers (own_rows, the filter
-    // gradient: the sum groups, and the long rows' sub-rows beside them), the generic kernel
-    // (long rows) and one launch per listed size class of the VALU kernels, spread over the
-    // side streams (largest work first, least-loaded stream)
+    // row pass: one or two launches for the rows the matrix cores take, or of fp32 grids one for
+    // every row that fits a thread's registers (own_rows, the filter gradient: the sum groups,
+    // and the long rows' sub-rows beside them), the generic kernel (long rows) and one launch
+    // per listed size class of the VALU kernels, spread over the side streams where they fork
+    // (largest work first, least-loaded stream)
     struct Launch {
         int cls;       // -1: generic kernel; >= 0: register-resident kernel of that class
         double work;
