@@ -55,8 +55,8 @@ struct HostPlan {
     std::vector<RowGroup> row_groups;
     std::vector<int64_t> row_group_points;  // per group: its documents' grid points
     std::vector<int32_t> row_blocks;
-    // forward and dx; filter gradient: sum groups, long rows.  Each one launch, or two, the longer
-    // rows first (add_launches)
+    // forward and dx; filter gradient: sum groups, long rows.  Each one launch, or two
+    // (add_launches)
     std::vector<RowLaunch> row_all, row_sum, row_own;
     // filter gradient outputs: the documents whose rows hold correlations after the row
     // pass (sum-group leaders and every document outside the sum groups), as copies of
