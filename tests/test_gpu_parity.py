@@ -545,3 +545,55 @@ def test_short_rows_beside_long_ones(device, monkeypatch):
     dxf, dkf = rc.packed_conv_backward(plan, x, dy, rc.filter_spectrum(plan, k))
     np.testing.assert_array_equal(dxf.float().cpu().numpy(), dx.astype(np.float32))
     assert rel_l2(dkf.cpu().numpy().astype(np.float64), refk) <= 5e-3
+
+
+@pytest.mark.parametrize("dtype, D, fork", [("f32", 70, "1"), ("bf16", 64, "1"), ("bf16", 64, "0"), ("bf16", 70, "1")])
+def test_captured_calls(device, monkeypatch, dtype, D, fork):
+    """The forward and the fused backward captured into a HIP graph, with the launches forked and
+    on one stream: every replay, with other inputs in the captured buffers and eager calls and
+    synchronisations between the replays, gives the eager calls' bits."""
+    import torch
+    import paper_2605_08451_amd as rc
+    monkeypatch.setenv("RUBICONV_DIRECT_MAX", "64")
+    monkeypatch.setenv("RUBICONV_FORK", fork)
+    rows = [[3, 64, 17, 200, 900, 1500, 2500, 41, 500] + [60] * 5, [20000], [18000, 1, 64]]
+    N = max(map(sum, rows))
+    rows = [r + [N - sum(r)] if sum(r) < N else r for r in rows]
+    W = wl.make_case(rows, D=D, L=N, x_dtype=dtype, seed=D + 1)
+    x0, k = to_device(W, device)
+    dy = torch.randn(x0.shape, generator=torch.Generator(device).manual_seed(2), device=device).to(x0.dtype)
+    plan = rc.Plan(W.cu_seqlens, N=N, D=D, L=N, x_dtype=dtype, y_dtype=dtype)
+    ws, dws, spec = plan.new_workspace(device), plan.new_dk_workspace(device), rc.filter_spectrum(plan, k)
+    x, y, dx = x0.clone(), torch.empty_like(x0), torch.empty_like(x0)
+    dk = torch.empty((D, N), device=device)
+
+    def calls():
+        rc.packed_conv(plan, x, spec, y=y, workspace=ws)
+        rc.packed_conv_backward(plan, x, dy, spec, dx=dx, dk=dk, workspace=dws)
+
+    scales = (1.0, 0.25, 8.0)
+    want = []
+    for s in scales:
+        x.copy_(x0 * s)
+        calls()
+        want.append([t.clone() for t in (y, dx, dk)])
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream):
+        calls()
+    torch.cuda.current_stream().wait_stream(stream)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        calls()
+    for turn in range(2):
+        for i, s in enumerate(scales):
+            x.copy_(x0 * s)
+            for t in (y, dx, dk):
+                t.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            for a, b in zip(want[i], (y, dx, dk)):
+                assert torch.equal(a, b), (turn, s)
+            rc.packed_conv(plan, x, spec, workspace=ws)   # eager work between the replays
+    torch.cuda.synchronize()
